@@ -59,8 +59,8 @@ def traffic_file(config, arch):
     return os.path.join(TRAFFIC_DIR, f"gemm_bf16_{config}_{arch}_traffic.md")
 
 
-TRAFFIC_SOURCES = ("paper_2510_14614_amd/csrc/gemm.hip", "paper_2510_14614_amd/csrc/kernels.h",
-                   "paper_2510_14614_amd/csrc/common.h")
+TRAFFIC_SOURCES = ("paper_2510_14614_amd/csrc/gemm.hip", "paper_2510_14614_amd/csrc/gemm_tiles.h",
+                   "paper_2510_14614_amd/csrc/kernels.h", "paper_2510_14614_amd/csrc/common.h")
 PEAK_BF16_TFLOPS = 2500.0  # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
 

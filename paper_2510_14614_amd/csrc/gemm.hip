@@ -13,112 +13,15 @@
 //    whole wavefront-tile rows.  Operands are addressed with 32-bit buffer
 //    offsets: every operand must span less than 2 GiB (the library's config
 //    check guarantees it; the launcher rejects anything else).
-//  * gemm_simt: fp32 FMA kernel (fp32 parity mode).
-// Every kernel launches all problems of a group in one grid, so the
+// (The fp32 mode's kernel is in gemm_f32.hip.)  Every kernel launches all problems of a group in one grid, so the
 // independent GEMMs of FAL's two branches can share a launch.
 #include <algorithm>
 
 #include "common.h"
+#include "gemm_tiles.h"
 #include "kernels.h"
 
 namespace fal {
-
-template <typename S>
-__device__ __forceinline__ void epilogue(const GemmProblem& P, int m, int n, float v, int gelu_tanh) {
-  if (m >= P.M || n >= P.N) return;
-  if (P.bias) v += to_f(static_cast<const S*>(P.bias)[n]);
-  if (P.bias2) v += to_f(static_cast<const S*>(P.bias2)[n]);
-  switch (P.epi) {
-    case EPI_STORE:
-      if (P.out_f32)
-        static_cast<float*>(P.out)[(int64_t)m * P.ldo + n] = v;
-      else
-        static_cast<S*>(P.out)[(int64_t)m * P.ldo + n] = from_f<S>(v);
-      break;
-    case EPI_GELU: {
-      float gv, dg;
-      gelu_and_grad(v, gelu_tanh, gv, dg);
-      if (P.out2) static_cast<S*>(P.out2)[(int64_t)m * P.ldo2 + n] = from_f<S>(dg);
-      static_cast<S*>(P.out)[(int64_t)m * P.ldo + n] = from_f<S>(gv);
-      break;
-    }
-    case EPI_RESID: {
-      float* o = static_cast<float*>(P.out) + (int64_t)m * P.ldo + n;
-      *o = P.resid[(int64_t)m * P.ldr + n] + v;
-      break;
-    }
-    case EPI_MUL_AUX: {
-      const float a = to_f(static_cast<const S*>(P.aux)[(int64_t)m * P.ldaux + n]);
-      static_cast<S*>(P.out)[(int64_t)m * P.ldo + n] = from_f<S>(v * a);
-      break;
-    }
-  }
-}
-
-// The problem owning workgroup `tile`, selected with constant indices so the
-// descriptor stays in scalar registers (a dynamic index into the by-value
-// array would copy it to scratch).
-__device__ __forceinline__ GemmProblem find_problem(const GemmGroup& g, int tile) {
-  static_assert(kMaxGroup == 4, "update find_problem");
-  if (g.n > 3 && tile >= g.p[3].tile_start) return g.p[3];
-  if (g.n > 2 && tile >= g.p[2].tile_start) return g.p[2];
-  if (g.n > 1 && tile >= g.p[1].tile_start) return g.p[1];
-  return g.p[0];
-}
-
-// ------------------------------------------------------------ SIMT (fp32) --
-constexpr int ST = 64, SK = 16;
-
-template <typename S, int AK, int BKM>
-__global__ __launch_bounds__(256) void gemm_simt(GemmGroup g, int gelu_tanh) {
-  __shared__ float As[SK][ST + 4];
-  __shared__ float Bs[SK][ST + 4];
-  const GemmProblem P = find_problem(g, blockIdx.x);
-  const int local = blockIdx.x - P.tile_start;
-  const int m0 = (local / P.tiles_n) * ST, n0 = (local % P.tiles_n) * ST;
-  const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-  float acc[4][4] = {};
-  for (int seg = 0; seg < 2; ++seg) {
-    const S* A = static_cast<const S*>(seg ? P.A2 : P.A);
-    const S* B = static_cast<const S*>(seg ? P.B2 : P.B);
-    const int64_t lda = seg ? P.lda2 : P.lda, ldb = seg ? P.ldb2 : P.ldb;
-    const int K = seg ? P.K2 : P.K;
-    for (int k0 = 0; k0 < K; k0 += SK) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int e = tid + 256 * i;
-        int mm, kk;
-        if (AK) { mm = e / SK; kk = e % SK; } else { kk = e / ST; mm = e % ST; }
-        const int m = m0 + mm, k = k0 + kk;
-        float v = 0.f;
-        if (m < P.M && k < K) v = to_f(A[AK ? (int64_t)m * lda + k : (int64_t)k * lda + m]);
-        As[kk][mm] = v;
-        int nn;
-        if (BKM) { nn = e / SK; kk = e % SK; } else { kk = e / ST; nn = e % ST; }
-        const int n = n0 + nn, k2 = k0 + kk;
-        float w = 0.f;
-        if (n < P.N && k2 < K) w = to_f(B[BKM ? (int64_t)n * ldb + k2 : (int64_t)k2 * ldb + n]);
-        Bs[kk][nn] = w;
-      }
-      __syncthreads();
-#pragma unroll
-      for (int kk = 0; kk < SK; ++kk) {
-        float a[4], b[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { a[i] = As[kk][ty * 4 + i]; b[i] = Bs[kk][tx * 4 + i]; }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-      }
-      __syncthreads();
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) epilogue<S>(P, m0 + ty * 4 + i, n0 + tx * 4 + j, acc[i][j], gelu_tanh);
-}
 
 // ----------------------------------------------------------- MFMA (bf16) --
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
@@ -362,24 +265,6 @@ __device__ __forceinline__ void store_staged(const GemmProblem& P, const f32x4_t
 #ifndef FAL_OCC3_KMAX
 #define FAL_OCC3_KMAX 1024  // longest K (both segments) sent to the three-workgroup kernel
 #endif
-#ifndef FAL_GEMM_GROUP_M
-#define FAL_GEMM_GROUP_M 4
-#endif
-constexpr int kXcds = 8, kGroupM = FAL_GEMM_GROUP_M;
-__device__ __forceinline__ int xcd_remap(int bid, int total) {
-  const int q = total / kXcds, r = total % kXcds;
-  const int xcd = bid % kXcds, slot = bid / kXcds;
-  return xcd < r ? xcd * (q + 1) + slot : r * (q + 1) + (xcd - r) * q + slot;
-}
-__device__ __forceinline__ void grouped_tile(int t, int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int band = kGroupM * tiles_n;
-  const int first = (t / band) * kGroupM;
-  const int gs = min(kGroupM, tiles_m - first);
-  const int in = t % band;
-  tm = first + in % gs;
-  tn = in / gs;
-}
-
 // ------------------------------------- MFMA (bf16), direct-to-LDS pipeline --
 // Four wavefronts (one per SIMD) own a BM x BN output tile as 2 x 2
 // wavefront tiles of (BM/2) x (BN/2).  K advances in slices of 32 (one
@@ -1004,6 +889,20 @@ __global__ __launch_bounds__(256) void splitk_reduce4(const float* part, int spl
   *reinterpret_cast<float4*>(out + (int64_t)m * ldo + n) = v;
 }
 
+// Sums a split problem's partials into its output.
+hipError_t splitk_sum(const GemmProblem& P, hipStream_t s) {
+  const bool v4 = P.N % 4 == 0 && P.ldo % 4 == 0 && reinterpret_cast<uintptr_t>(P.out) % 16 == 0;
+  if (v4)
+    hipLaunchKernelGGL(splitk_reduce4, dim3(cdiv((int64_t)P.M * P.N / 4, 256)), dim3(256), 0, s, P.part, P.splits, P.M,
+                       P.N, static_cast<const bf16*>(P.bias), static_cast<const bf16*>(P.bias2),
+                       static_cast<float*>(P.out), P.ldo);
+  else
+    hipLaunchKernelGGL(splitk_reduce, dim3(cdiv((int64_t)P.M * P.N, 256)), dim3(256), 0, s, P.part, P.splits, P.M, P.N,
+                       static_cast<const bf16*>(P.bias), static_cast<const bf16*>(P.bias2),
+                       static_cast<float*>(P.out), P.ldo);
+  return hipGetLastError();
+}
+
 constexpr int kCUs = 256;
 constexpr int kMaxSplits = 16;
 
@@ -1169,24 +1068,6 @@ hipError_t gemm(DType dt, int a_kmaj, int b_kmaj, GemmGroup& g, int gelu_tanh, h
     }
     return total;
   };
-  auto launch_reduce = [&]() -> hipError_t {
-    const GemmProblem& P = g.p[0];
-    if (g.n == 1 && P.splits > 1) {
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      const bool v4 = P.N % 4 == 0 && P.ldo % 4 == 0 && reinterpret_cast<uintptr_t>(P.out) % 16 == 0;
-      if (v4)
-        hipLaunchKernelGGL(splitk_reduce4, dim3(cdiv((int64_t)P.M * P.N / 4, 256)), dim3(256), 0, s, P.part,
-                           P.splits, P.M, P.N, static_cast<const bf16*>(P.bias), static_cast<const bf16*>(P.bias2),
-                           static_cast<float*>(P.out), P.ldo);
-      else
-        hipLaunchKernelGGL(splitk_reduce, dim3(cdiv((int64_t)P.M * P.N, 256)), dim3(256), 0, s, P.part, P.splits,
-                           P.M, P.N, static_cast<const bf16*>(P.bias), static_cast<const bf16*>(P.bias2),
-                           static_cast<float*>(P.out), P.ldo);
-    }
-    return hipGetLastError();
-  };
-
   if (dt == BF16 && pipe_ok(g, a_kmaj, b_kmaj)) {
     int shape, sp;
     choose_pipe(g, splittable, splitk_floats, shape, sp);
@@ -1245,7 +1126,8 @@ hipError_t gemm(DType dt, int a_kmaj, int b_kmaj, GemmGroup& g, int gelu_tanh, h
     }
 #undef FAL_DBL_LAUNCH
 #undef FAL_PIPE_LAUNCH
-    return launch_reduce();
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess || sp == 1 ? e : splitk_sum(g.p[0], s);
   }
 
   if (dt == BF16) {
@@ -1255,14 +1137,7 @@ hipError_t gemm(DType dt, int a_kmaj, int b_kmaj, GemmGroup& g, int gelu_tanh, h
            "zero padding)";
     return hipErrorInvalidValue;
   }
-  const int total = set_tiles(ST, ST);
-  g.total_tiles = total;
-  const dim3 grid(total), block(256);
-  if (a_kmaj && b_kmaj) hipLaunchKernelGGL((gemm_simt<float, 1, 1>), grid, block, 0, s, g, gelu_tanh);
-  else if (a_kmaj) hipLaunchKernelGGL((gemm_simt<float, 1, 0>), grid, block, 0, s, g, gelu_tanh);
-  else if (b_kmaj) hipLaunchKernelGGL((gemm_simt<float, 0, 1>), grid, block, 0, s, g, gelu_tanh);
-  else hipLaunchKernelGGL((gemm_simt<float, 0, 0>), grid, block, 0, s, g, gelu_tanh);
-  return hipGetLastError();
+  return gemm_f32(a_kmaj, b_kmaj, g, gelu_tanh, s, splitk_scratch, splitk_floats);
 }
 
 }  // namespace fal
