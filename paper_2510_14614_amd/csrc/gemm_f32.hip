@@ -20,17 +20,18 @@
 // Measured, launches repeated on three operand sets (in brackets the average
 // launch of the FMA kernel of 64 x 64 tiles this replaces, from a kernel trace
 // of whole steps at the same widths; there two streams shared the chip):
-//  * 64 tokens, d 64, f 256: 5.1 us (1, 0), 5.6 us (1, 1), 4.6 us (0, 0)
+//  * 64 tokens, d 64, f 256: 5.0 us (1, 0), 5.6 us (1, 1), 4.3 us (0, 0)
 //    [27.4, 24.3, 14.3];
-//  * 2048 tokens, d 768, f 3072: QKV 96 us (75 TFLOP/s), FFN up with GELU 122
-//    (79), down projection 169 (57) [312]; data gradients 139 (69), 131 (74)
-//    and 89 (81) [326]; weight gradients 126 (58), 121 (80) and 50 (48) [409];
-//  * 8192 x 8192 x 2048: 117 TFLOP/s in every orientation.
+//  * 2048 tokens, d 768, f 3072: QKV 87 us (83 TFLOP/s), FFN up with GELU 104
+//    (93), down projection 154 (63) [312]; data gradients 116 (83), 108 (89)
+//    and 84 (86) [326]; weight gradients 111 (87), 85 (85) and 37 (65) [409];
+//  * 4096 x 4096 x 4096: 117 TFLOP/s in every orientation.
 // Rounding: one fp32 FMA per product as before, in another order of k; against
 // fp64 on normal data the two orders' sums are equally far off (1.5e-7 at
 // K = 64, 1.0e-6 at 3072, by emulation of both orders), split ones nearer
 // (5.5e-7 at K = 3072 in three).
 #include <algorithm>
+#include <cstring>
 
 #include "common.h"
 #include "gemm_tiles.h"
@@ -266,32 +267,52 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma(GemmGroup g, int gelu_ta
 
 namespace {
 
-struct Shape { int bm, bn, ks; double eff, ovh; };
-enum { S128 = 0, S128x64 = 1, S64 = 2, S32 = 3, kShapes = 4 };
-// share of the MFMA rate a full chip reaches on the shape, and fixed us per
-// launch.  Smaller tiles read more operand bytes per flop and pay the fixed
-// cost of a slice for less work, but leave fewer CUs idle in the last round:
-// 2048 x 768 x 768 has 96 tiles of 128 x 128 and 384 of 64 x 64 for 256 CUs.
-// The shares are estimates; the launches they choose reach 48 to 81 TFLOP/s of
-// 157 at the sizes above, 117 where whole rounds of 128 x 128 fill the chip.
-constexpr Shape kShape[kShapes] = {{128, 128, 32, 0.80, 4.0}, {128, 64, 32, 0.78, 3.0}, {64, 64, 32, 0.72, 3.0},
-                                   {32, 32, 128, 0.40, 2.5}};
+// Launch time model, as the bf16 launcher's: a K slice of one tile costs t1 us
+// when its CU holds that workgroup alone and t2 us when the CU holds all
+// per_cu it has LDS for (in between, in proportion), each round of tiles adds
+// ovh us (first loads, epilogue) and the launch kLaunchUs; a K split adds the
+// reduce launch and its partials, written and read back.
+//
+// Fitted to the launch times of 325 problems on MI355X (each tile shape, splits
+// up to 16 where the scratch holds them; 16 to 8192 tokens, widths 32 to 8192
+// and a 50257-wide head, the three orientations of a step): the chosen launch
+// is 1% slower on average than the fastest of its problem and 25% at worst
+// (with assumed shares of the MFMA rate and rounds of 256 tiles it was 8% and
+// 100%), and the estimate is off by 6% in the median, 17% for nine in ten.
+// What decides between the shapes is how the tiles fill the CUs: per flop a
+// full CU takes t2 / per_cu, 1.38, 1.49 and 2.39 times the MFMA's time, but
+// 2048 x 768 x 768 has 96 tiles of 128 x 128 (73 us), 384 of 64 x 64 (43 us)
+// and 1536 of 32 x 32 (46 us).  128 x 64 was the fastest by 3% at most and the
+// fitted rule never took it, so the kernel has no such shape.
+struct Shape { int bm, bn, ks, per_cu; double t1, t2, ovh; };
+enum { S128 = 0, S64 = 1, S32 = 2, kShapes = 3 };
+constexpr Shape kShape[kShapes] = {{128, 128, 32, 2, 2.8, 4.7, 3.3},
+                                   {64, 64, 32, 4, 1.07, 2.55, 1.25},
+                                   {32, 32, 128, 2, 1.6, 2.04, 0.9}};
 constexpr int kCUs = 256, kMaxSplits = 16;
-constexpr double kFlopsPerUsCU = 256.0 * 2400.0;
-constexpr double kPartialBytesPerUs = 5.0e6, kReduceUs = 5.0;
+// shortest K a split may get, two slices of 32 (measured over 154 problems: with
+// 256 the choice is 2.6% off the fastest on average, with 128 1.6%, with 64 1.1%)
+constexpr int kMinSplitK = 64;
+constexpr double kLaunchUs = 3.2, kReduceUs = 1.8, kPartialBytesPerUs = 6.8e6;
+
+int slices(const Shape& t, int K) { return (K + t.ks - 1) / t.ks; }
 
 double estimate(const GemmGroup& g, int c, int sp) {
   const Shape& t = kShape[c];
   int64_t tiles = 0;
-  double work = 0.0;  // longest tile's flops
+  int ns = 0;  // longest tile's slices, whole ones as the kernel hands them out
   for (int i = 0; i < g.n; ++i) {
     const GemmProblem& P = g.p[i];
     tiles += (int64_t)((P.M + t.bm - 1) / t.bm) * ((P.N + t.bn - 1) / t.bn) * sp;
-    work = std::max(work, 2.0 * t.bm * t.bn * ((double)(P.K + P.K2) / sp));
+    ns = std::max(ns, (slices(t, P.K) + sp - 1) / sp + slices(t, P.K2));
   }
-  const double rounds = (double)((tiles + kCUs - 1) / kCUs);
-  double us = t.ovh + rounds * work / kFlopsPerUsCU / t.eff;
-  if (sp > 1) us += (2.0 * sp + 1.0) * 4.0 * g.p[0].M * g.p[0].N / kPartialBytesPerUs + kReduceUs;
+  const int64_t slots = (int64_t)t.per_cu * kCUs, rem = tiles % slots;
+  double us = kLaunchUs + (double)(tiles / slots) * (t.ovh + ns * t.t2);
+  if (rem > 0) {
+    const int q = (int)((rem + kCUs - 1) / kCUs);  // workgroups per CU in the last round
+    us += t.ovh + ns * (t.t1 + (t.t2 - t.t1) * (q - 1) / (t.per_cu - 1));
+  }
+  if (sp > 1) us += kReduceUs + (2.0 * sp + 1.0) * 4.0 * g.p[0].M * g.p[0].N / kPartialBytesPerUs;
   return us;
 }
 
@@ -304,22 +325,32 @@ void launch(int a_kmaj, int b_kmaj, const GemmGroup& g, int gelu_tanh, hipStream
   else hipLaunchKernelGGL((gemm_f32_mfma<0, 0, BM, BN, KS>), grid, block, 0, s, g, gelu_tanh);
 }
 
+// The shape (and, for a single plain product, the K split) with the smallest
+// estimated time.  A split takes ceil(slices / splits) whole slices, and the
+// estimate counts them so: a count that leaves the last splits none (35 slices
+// in 16 splits of 3, which 12 cover) never beats the smaller one that does not.
+double choose(const GemmGroup& g, bool splittable, int64_t splitk_floats, int& shape, int& splits) {
+  const GemmProblem& P0 = g.p[0];
+  double best = 0.0;
+  shape = -1;
+  splits = 1;
+  for (int c = 0; c < kShapes; ++c)
+    for (int sp = 1; sp <= (splittable ? kMaxSplits : 1); ++sp) {
+      if (sp > 1 && (P0.K / sp < kMinSplitK || (int64_t)sp * P0.M * P0.N > splitk_floats)) break;
+      const double us = estimate(g, c, sp);
+      if (shape < 0 || us < best) { best = us; shape = c; splits = sp; }
+    }
+  return best;
+}
+
 }  // namespace
 
-// The tile shape (and, for a single plain product, the K split) with the
-// smallest estimated time.
 hipError_t gemm_f32(int a_kmaj, int b_kmaj, GemmGroup& g, int gelu_tanh, hipStream_t s, float* splitk_scratch,
                     int64_t splitk_floats) {
   const GemmProblem& P0 = g.p[0];
   const bool splittable = splitk_scratch && g.n == 1 && P0.K2 == 0 && P0.epi == EPI_STORE && !P0.bias && !P0.bias2;
-  double best = 0.0;
-  int shape = -1, splits = 1;
-  for (int c = 0; c < kShapes; ++c)
-    for (int sp = 1; sp <= (splittable ? kMaxSplits : 1); ++sp) {
-      if (sp > 1 && (P0.K / sp < 256 || (int64_t)sp * P0.M * P0.N > splitk_floats)) break;
-      const double us = estimate(g, c, sp);
-      if (shape < 0 || us < best) { best = us; shape = c; splits = sp; }
-    }
+  int shape, splits;
+  choose(g, splittable, splitk_floats, shape, splits);
   const Shape& t = kShape[shape];
   int total = 0;
   for (int i = 0; i < g.n; ++i) {
@@ -337,12 +368,32 @@ hipError_t gemm_f32(int a_kmaj, int b_kmaj, GemmGroup& g, int gelu_tanh, hipStre
   g.total_tiles = total;
   switch (shape) {
     case S128: launch<128, 128, 32>(a_kmaj, b_kmaj, g, gelu_tanh, s); break;
-    case S128x64: launch<128, 64, 32>(a_kmaj, b_kmaj, g, gelu_tanh, s); break;
     case S64: launch<64, 64, 32>(a_kmaj, b_kmaj, g, gelu_tanh, s); break;
     default: launch<32, 32, 128>(a_kmaj, b_kmaj, g, gelu_tanh, s); break;
   }
   const hipError_t e = hipGetLastError();
   return e != hipSuccess || splits == 1 ? e : splitk_sum(g.p[0], s);
+}
+
+// The launcher's choice for one problem, for host tests (not part of the C
+// ABI): out = {tile rows, tile columns, K slice, splits}; returns the
+// estimated us.
+extern "C" double fal_gemm_f32_choice(int32_t M, int32_t N, int32_t K, int32_t K2, int32_t splittable,
+                                      int64_t splitk_floats, int32_t* out) {
+  GemmGroup g;
+  memset(&g, 0, sizeof(g));
+  g.n = 1;
+  g.p[0].M = M;
+  g.p[0].N = N;
+  g.p[0].K = K;
+  g.p[0].K2 = K2;
+  int shape, splits;
+  const double us = choose(g, splittable && K2 == 0, splitk_floats, shape, splits);
+  out[0] = kShape[shape].bm;
+  out[1] = kShape[shape].bn;
+  out[2] = kShape[shape].ks;
+  out[3] = splits;
+  return us;
 }
 
 }  // namespace fal
