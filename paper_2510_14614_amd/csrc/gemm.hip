@@ -1137,6 +1137,10 @@ hipError_t gemm(DType dt, int a_kmaj, int b_kmaj, GemmGroup& g, int gelu_tanh, h
            "zero padding)";
     return hipErrorInvalidValue;
   }
+  if (!a_kmaj && b_kmaj) {
+    *why = "fp32 GEMM with a strided A and a k-contiguous B";
+    return hipErrorInvalidValue;
+  }
   return gemm_f32(a_kmaj, b_kmaj, g, gelu_tanh, s, splitk_scratch, splitk_floats);
 }
 

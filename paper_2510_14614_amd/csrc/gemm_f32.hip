@@ -316,12 +316,12 @@ double estimate(const GemmGroup& g, int c, int sp) {
   return us;
 }
 
+// (a step has no product with a strided A and a k-contiguous B; gemm() refuses it)
 template <int BM, int BN, int KS>
 void launch(int a_kmaj, int b_kmaj, const GemmGroup& g, int gelu_tanh, hipStream_t s) {
   const dim3 grid(g.total_tiles), block(256);
   if (a_kmaj && b_kmaj) hipLaunchKernelGGL((gemm_f32_mfma<1, 1, BM, BN, KS>), grid, block, 0, s, g, gelu_tanh);
   else if (a_kmaj) hipLaunchKernelGGL((gemm_f32_mfma<1, 0, BM, BN, KS>), grid, block, 0, s, g, gelu_tanh);
-  else if (b_kmaj) hipLaunchKernelGGL((gemm_f32_mfma<0, 1, BM, BN, KS>), grid, block, 0, s, g, gelu_tanh);
   else hipLaunchKernelGGL((gemm_f32_mfma<0, 0, BM, BN, KS>), grid, block, 0, s, g, gelu_tanh);
 }
 
