@@ -107,7 +107,7 @@ const char* validate_hd(const fal_config_t* c) {
 // the M token rows) is read up to 256 rows past its end inside that range.
 // So every [M, width] operand of the step -- the saved activations [M, d],
 // [M, dA + 2 dKV], [M, dA + f] and the logits [M, V] -- must span less than
-// 2 GiB including those rows.  (The fp32 parity path indexes with 64 bits.)
+// 2 GiB including those rows.  (The fp32 GEMM indexes with 64 bits.)
 const char* validate_extent(const fal_config_t* c) {
   if (c->dtype != FAL_BF16) return nullptr;
   const Dims D = dims_of(*c);
@@ -268,8 +268,9 @@ void carve(const fal_config_t& c, char* base, Work& W, size_t* total) {
   W.part_main = cv.take<float>(part);
   W.part_aux = cv.take<float>(part);
   W.bias_part = cv.take<float>(col_sum_batch_scratch((int)M, (int)(2 * d + D.f + D.dqkv)));
-  // a split is only chosen while fewer than 512 output tiles of 128x128
-  // exist, so (512 + 512) tiles of partials bound every split decision
+  // bf16 splits pay only while fewer than 512 output tiles of 128x128 exist,
+  // so partials of (512 + 512) of them hold any worth having; the launchers
+  // (bf16 and fp32) take no split whose partials exceed this
   W.splitk_floats = (int64_t)1024 * 128 * 128;
   W.splitk_main = cv.take<float>(W.splitk_floats);
   W.splitk_aux = cv.take<float>(W.splitk_floats);
@@ -529,6 +530,7 @@ struct Run {
       // fills them; when the QKV GEMM fills whole rounds, the FFN-up GEMM
       // goes after it and overlaps the attention kernel (whose causal tail
       // leaves compute units idle) instead of splitting the CUs with it.
+      // In fp32 the fill is not modelled and reads as whole rounds.
       hipStream_t s2 = sm;
       const GemmProblem pq = qkv_prob(S, bp);
       bool fc_first = true;

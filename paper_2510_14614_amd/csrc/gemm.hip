@@ -13,8 +13,9 @@
 //    whole wavefront-tile rows.  Operands are addressed with 32-bit buffer
 //    offsets: every operand must span less than 2 GiB (the library's config
 //    check guarantees it; the launcher rejects anything else).
-// (The fp32 mode's kernel is in gemm_f32.hip.)  Every kernel launches all problems of a group in one grid, so the
-// independent GEMMs of FAL's two branches can share a launch.
+// The fp32 mode's kernel is in gemm_f32.hip.  Every kernel launches all
+// problems of a group in one grid, so the independent GEMMs of FAL's two
+// branches can share a launch.
 #include <algorithm>
 
 #include "common.h"

@@ -64,18 +64,21 @@ struct GemmGroup {
 
 // Launches every problem of `g` (same dtype and operand orientation) as one
 // grouped kernel.  Problems that would leave most compute units idle (few
-// output tiles, long K, fp32 EPI_STORE output, single K segment) have their
-// K range split across workgroups: each slice writes fp32 partials to
+// output tiles, long K, fp32 EPI_STORE output, single K segment, and in an
+// fp32 launch no bias, which the reduce reads as bf16) have their K range
+// split across workgroups: each slice writes fp32 partials to
 // `splitk_scratch` and a second kernel sums the slices in a fixed order, so
-// results stay deterministic.  splitk_floats: capacity of the scratch (0
-// disables splitting).  Returns hipSuccess or the launch error; `why`
-// receives a static message for argument errors.
+// results stay deterministic.  splitk_floats: capacity of the scratch, which
+// no split exceeds (0 disables splitting).  a_kmaj = 0 with b_kmaj = 1 is for
+// bf16 only.  Returns hipSuccess or the launch error; `why` receives a static
+// message for argument errors.
 hipError_t gemm(DType dt, int a_kmaj, int b_kmaj, GemmGroup& g, int gelu_tanh, hipStream_t s,
                 const char** why, float* splitk_scratch = nullptr, int64_t splitk_floats = 0);
 // The share of the chip's workgroup slots the launch of `g` would occupy
 // in its last round (1.0 when its tiles fill whole rounds; 1.0 as well for
-// launches off the matrix-core path).  Lets a scheduler tell whether
-// another launch can use compute units this one leaves idle.
+// fp32 launches and for arguments gemm() refuses).  Lets a scheduler tell
+// whether another launch can use compute units this one leaves idle; an fp32
+// launch always reads as full, so what follows it stays behind it.
 double gemm_last_round_fill(DType dt, int a_kmaj, int b_kmaj, const GemmGroup& g, int64_t splitk_floats);
 
 // ----------------------------------------------------------- LayerNorm ----
