@@ -5,6 +5,8 @@ import random
 
 from paper_2510_14614_amd import fal
 
+import test_gpu_f32_gemm as gpu_tests
+
 SCRATCH = 1024 * 128 * 128  # floats of split-K scratch a context gives each stream
 
 
@@ -104,3 +106,17 @@ def test_estimate_is_near_the_measured_launch():
         errors.append(abs(math.log(us / times[bm, sp])))
     errors.sort()
     assert errors[len(errors) // 2] <= 0.1 and errors[len(errors) * 9 // 10] <= 0.25, errors
+
+
+def test_gpu_steps_cover_every_tile():
+    taken = set()
+    for stack in gpu_tests.STACKS:
+        for name, (M, N, K, K2, may_split) in gpu_tests.PRODUCTS(*stack).items():
+            (bm, _, _, sp), _ = choice(M, N, K, K2, splittable=bool(may_split))
+            kind = "weight gradient" if name.startswith("dW") else "data gradient" if name.startswith("dH") else name
+            taken.add((kind, bm, sp > 1))
+    need = {(kind, bm, False) for bm in (32, 64, 128)
+            for kind in ("ffn up, GELU", "projection, residual", "ffn up gradient, GELU'", "data gradient")}
+    need |= {("weight gradient", bm, True) for bm in (32, 64, 128)}
+    need |= {("data gradient", bm, True) for bm in (32, 64)}
+    assert need <= taken, need - taken
