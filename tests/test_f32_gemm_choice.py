@@ -111,7 +111,7 @@ def test_estimate_is_near_the_measured_launch():
 def test_gpu_steps_cover_every_tile():
     taken = set()
     for stack in gpu_tests.STACKS:
-        for name, (M, N, K, K2, may_split) in gpu_tests.PRODUCTS(*stack).items():
+        for name, (M, N, K, K2, may_split) in gpu_tests.products(*stack).items():
             (bm, _, _, sp), _ = choice(M, N, K, K2, splittable=bool(may_split))
             kind = "weight gradient" if name.startswith("dW") else "data gradient" if name.startswith("dH") else name
             taken.add((kind, bm, sp > 1))

@@ -2,7 +2,7 @@
 counts where its launcher takes each of its tile shapes, with and without a K
 split, under each epilogue.
 
-``PRODUCTS`` names a block's products and ``STACKS`` the steps; the host test
+``products`` names a block's products and ``STACKS`` the steps; the host test
 ``test_gpu_steps_cover_every_tile`` (test_f32_gemm_choice.py) holds them to
 the launcher's choice, so that a change of its rule cannot drop the coverage
 unseen.  Widths are multiples of 8 that no tile divides, token counts are
@@ -29,7 +29,7 @@ STACKS = [(136, 2, 16, 328, 300, 3), (328, 4, 16, 840, 300, 4), (520, 8, 64, 205
           (1032, 16, 64, 264, 1065, 2)]   # that projection on 64 x 64, a weight gradient split on 128 x 128
 
 
-def PRODUCTS(d, heads, hd, f, seq, batch):
+def products(d, heads, hd, f, seq, batch):
     """{product: (M, N, K, K2, may split)} of a block with its branches on streams."""
     M, dA = batch * seq, heads * hd
     return {"qkv": (M, 3 * dA, d, 0, 0), "ffn up, GELU": (M, f, d, 0, 0), "projection, residual": (M, d, dA, f, 0),
